@@ -159,6 +159,21 @@ def test_score_gradient_narrow_heads(heads, dh):
             check_sddmm_softmax_backward(csr, G, x, dy, s, plan=plan, leaky=leaky)
 
 
+@pytest.mark.parametrize("dh", [4, 8, 16])
+def test_score_gradient_twelve_heads(dh):
+    """Twelve heads: a multiple of four that does not divide a wavefront's 256
+    values, so that no lane keeps its heads along a row."""
+    csr = _graph(dh, 60, 60, 0, 150)
+    G = fg.Graph.from_csr(csr)
+    rng = np.random.default_rng(dh)
+    x = rng.integers(-3, 4, (csr.num_cols, 12, dh)).astype(np.float32)
+    dy = rng.integers(-3, 4, (csr.num_rows, 12, dh)).astype(np.float32)
+    s = (3 * rng.standard_normal((csr.nnz, 12))).astype(np.float32)
+    for plan in (None, fg.Plan(G, 12 * dh), fg.Plan(G, 12 * dh, segment_edges=64)):
+        for leaky in (True, False):
+            check_sddmm_softmax_backward(csr, G, x, dy, s, plan=plan, leaky=leaky)
+
+
 @pytest.mark.parametrize("d", [4, 16, 20, 32, 64, 128, 256, 512, 1024])
 def test_fused_scores_and_softmax(d):
     """One pass for scores and weights on plans of short items and without a
