@@ -121,6 +121,7 @@ constexpr int kDppRowHalfMirror = 0x141;
 constexpr int kDppRowMirror = 0x140;
 constexpr int kDppRowBcast15 = 0x142;   // lane 15 of each row -> next row
 constexpr int kDppRowBcast31 = 0x143;   // lane 31 -> rows 2 and 3
+constexpr int kDppWaveShr1 = 0x138;     // lane l - 1 -> lane l
 
 template <int CTRL, int ROW_MASK = 0xF>
 __device__ __forceinline__ float dpp_f(float v) {
@@ -341,7 +342,7 @@ __device__ __forceinline__ void wide_get(const T* tab, int gid, int j0, T (&out)
 // unsorted rows only have fewer runs to merge.)
 __device__ __forceinline__ int batch_runs(const int32_t (&id)[4], int lane, int cnt,
                                           bool (&head)[4], int (&run)[4]) {
-  const int before = __shfl_up(id[3], 1);
+  const int before = __builtin_amdgcn_update_dpp(0, id[3], kDppWaveShr1, 0xF, 0xF, false);
   int n = 0, total = 0;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -358,6 +359,41 @@ __device__ __forceinline__ int batch_runs(const int32_t (&id)[4], int lane, int 
     run[q] = n - 1;
   }
   return total;
+}
+
+// Sums of v over the runs of a batch, in an order that the batch alone fixes
+// (lane l holding edges 4l .. 4l + 3, runs as batch_runs numbers them):
+// sum[q] is the run's sum where last[q], at the run's last edge.  Each lane adds
+// its own elements of a run in edge order; the parts of a run that spans lanes
+// then meet in steps of 1, 2, 4, ... lanes, as many as the longest run needs.
+__device__ __forceinline__ void run_sums(const float (&v)[4], const bool (&head)[4], int lane,
+                                         int cnt, float (&sum)[4], bool (&last)[4]) {
+  sum[0] = v[0];
+#pragma unroll
+  for (int q = 1; q < 4; ++q) sum[q] = head[q] ? v[q] : sum[q - 1] + v[q];
+  // lanes between this one and the lane where its last run starts (lanes past
+  // the batch hold zeros and count as starting one)
+  const bool starts = head[0] || head[1] || head[2] || head[3] || 4 * lane >= cnt;
+  const uint64_t firsts = __ballot(head[0]), m = __ballot(starts);
+  const int back = __clzll((long long)(m << (63 - lane)));
+  float t = sum[3];
+  const float below = dpp_f<kDppWaveShr1>(t);
+  if (back >= 1) t = below + t;
+  for (int d = 2; d < kWave; d <<= 1) {
+    if (__ballot(back >= d) == 0) break;  // wave-uniform
+    const float o = __shfl_up(t, d);
+    if (back >= d) t = o + t;
+  }
+  const float before = dpp_f<kDppWaveShr1>(t);
+  bool whole = false;  // the run started in this lane
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int k = 4 * lane + q;
+    whole = whole || head[q];
+    const bool next = q < 3 ? head[(q + 1) & 3] : lane < kWave - 1 && (firsts >> (lane + 1)) & 1;
+    last[q] = k < cnt && (k == cnt - 1 || next);
+    if (!whole) sum[q] = before + sum[q];
+  }
 }
 
 // Key by which the copies of a weighted edge merge (q: the edge's place in its

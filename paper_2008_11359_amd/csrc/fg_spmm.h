@@ -145,8 +145,8 @@ __device__ __forceinline__ void spmm_store(const SpmmParams& p, const Item& it, 
 //
 // DUP (wide batches): graphs that repeat many edges.  Copies of an edge are
 // neighbours in a row, so each batch is packed to one entry per run of equal
-// sources before its gathers: their weights (1 for copies) add up in the table,
-// and the max keeps a run's first edge.  On the power-law graph, where 32% of
+// sources before its gathers: their weights (1 for copies) are added in a fixed
+// order (run_sums), and the max keeps a run's first edge.  On the power-law graph, where 32% of
 // the edges repeat another, the address unit then serves as many fewer
 // gathers: weighted sum 2224 -> 2002 us, max 2202 -> 1997.
 template <int G, int NV, int U, bool MUL, bool MAX, bool EIDS, bool SEG, bool ADD, int HM,
@@ -305,11 +305,17 @@ __global__ __launch_bounds__(kBlock, (WIDE && !MUL && NV == 1) ? 7 : 1) void spm
         } else {
           cnt = batch_runs(qs, lane, edges, head, run);
         }
-        wave_lds_sync();  // the previous batch's table reads are done
+        float w4[4], sum[4];
+        bool last[4];
         if constexpr (WGT) {
-          for (int i = lane; i < WT; i += kWave) wwt[i] = 0.0f;
-          wave_lds_sync();
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            if constexpr (MUL) w4[q] = __builtin_bit_cast(float, qw[q]);
+            else w4[q] = 4 * lane + q < edges ? 1.0f : 0.0f;
+          }
+          run_sums(w4, head, lane, edges, sum, last);
         }
+        wave_lds_sync();  // the previous batch's table reads are done
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int at = wide_at<NG>(run[q]);
@@ -318,8 +324,7 @@ __global__ __launch_bounds__(kBlock, (WIDE && !MUL && NV == 1) ? 7 : 1) void spm
             if constexpr (MAX) wk[at] = 4 * lane + q;
           }
           if constexpr (WGT) {
-            if (4 * lane + q < edges)
-              atomicAdd(&wwt[at], MUL ? __builtin_bit_cast(float, qw[q]) : 1.0f);
+            if (last[q]) wwt[at] = sum[q];
           }
         }
       } else {

@@ -307,3 +307,56 @@ def test_repeated_edges_weights(d, w):
     fin = np.isfinite(ref)
     # 512 float sums of one-signed terms, or of two terms against the rest
     np.testing.assert_allclose(y[fin], ref[fin], rtol=512 * 2.0**-24, atol=512 * 2.0**-24 * 2.0**-30)
+
+
+def _run_sums(keys, w):
+    """Weights of each run of equal keys in a batch of 256 edges, added as the
+    kernel states it: four neighbouring edges in order, then lanes by steps of
+    1, 2, 4, ... (float32)."""
+    f = np.float32
+    start = np.r_[True, keys[1:] != keys[:-1]]
+    head = start.reshape(64, 4)
+    part = w.reshape(64, 4).astype(f).copy()
+    for q in range(1, 4):
+        part[:, q] = np.where(head[:, q], part[:, q], f(part[:, q - 1] + part[:, q]))
+    starts = head.any(1)
+    back = np.array([next(b for b in range(64) if starts[l - b]) for l in range(64)])
+    t = part[:, 3].copy()
+    for d in (1, 2, 4, 8, 16, 32):
+        o = np.r_[np.zeros(d, f), t[:-d]]
+        t = np.where(back >= d, f(o + t), t)
+    before = np.r_[f(0), t[:-1]]
+    whole = np.logical_or.accumulate(head, axis=1)
+    part = np.where(whole, part, f(before[:, None] + part))
+    return keys[start], part.reshape(-1)[np.r_[np.nonzero(start)[0][1:] - 1, 255]]
+
+
+@pytest.mark.parametrize("d", [72, 128])
+def test_repeated_edges_order(d):
+    """The weights of an edge's copies are added in the order that the kernel
+    states, whatever the hardware does: with unit features of one column per
+    source, each output is one run's sum, bit for bit, on every call."""
+    rng = np.random.default_rng(d)
+    n, m = 128, d
+    src = np.concatenate([np.sort(rng.integers(0, rng.integers(1, m + 1), 256)) for _ in range(n)])
+    csr = synth.coo_to_csr(np.repeat(np.arange(n), 256).astype(np.int64), src.astype(np.int64), n, m)
+    w = (rng.random(csr.nnz) + 0.01).astype(np.float32)
+    want = np.zeros((n, m), np.float32)
+    for r in range(n):
+        k, v = _run_sums(csr.indices[256 * r:256 * r + 256], w[256 * r:256 * r + 256])
+        want[r, k] = v
+    G = fg.Graph.from_csr(csr)
+    plan = fg.Plan(G, d, segment_edges=256)
+    x, w = dev(np.eye(m, dtype=np.float32)), dev(w)
+    for _ in range(3):
+        y = host(fg.gspmm(G, x, w, msg="src_mul_edge", plan=plan))
+        np.testing.assert_array_equal(y, want)
+    # rows in pieces, any features: call to call, and without allocation
+    plan = fg.Plan(G, d, segment_edges=150, item_order=1)
+    x = dev(rng.standard_normal((m, d)).astype(np.float32))
+    y = host(fg.gspmm(G, x, w, msg="src_mul_edge", plan=plan))
+    out = dev(np.zeros((n, d), np.float32))
+    for _ in range(3):
+        np.testing.assert_array_equal(host(fg.gspmm(G, x, w, msg="src_mul_edge", plan=plan)), y)
+        fg.gspmm_noalloc(G, x, out, edge=w, msg="src_mul_edge", plan=plan)
+        np.testing.assert_array_equal(host(out), y)
