@@ -1278,7 +1278,7 @@ fg_status fg_edge_softmax(const fg_graph* g, int32_t num_heads, const float* sco
   if (out != scores && overlaps(out, b, scores, b)) return FG_ERR_INVALID_ARG;
   const fg::GraphView gv = view_of(g);
   return from_hip(fg::launch_edge_softmax(gv, plan ? &plan->plain : nullptr, num_heads, scores,
-                                          apply_leaky_relu != 0, negative_slope, out,
+                                          apply_leaky_relu != 0, negative_slope, out, false,
                                           static_cast<hipStream_t>(stream)));
 }
 
@@ -1332,7 +1332,8 @@ fg_status fg_gsddmm_edge_softmax(const fg_graph* g, int32_t num_heads, int64_t h
       plan && g->nnz >= (plan->gather.num_split_rows > 0 ? fg::kTwoPassItemEdges
                                                          : fg::kTwoPassWholeRowEdges) *
                             std::max<int64_t>(plan->gather.num_segments, 1);
-  if (!long_items && fg::gsddmm_softmax_fused(num_heads, head_dim, x_src, x_dst))
+  const bool fused = fg::gsddmm_softmax_fused(num_heads, head_dim, x_src, x_dst);
+  if (!long_items && fused)
     return from_hip(fg::launch_gsddmm_softmax(gv, plan ? &plan->gather : nullptr, F, x_src, x_dst,
                                               apply_leaky_relu != 0, negative_slope, scores, out,
                                               hs));
@@ -1341,7 +1342,7 @@ fg_status fg_gsddmm_edge_softmax(const fg_graph* g, int32_t num_heads, int64_t h
                                    x_dst, scores, hs);
   if (e != hipSuccess) return FG_ERR_HIP;
   return from_hip(fg::launch_edge_softmax(gv, plan ? &plan->plain : nullptr, num_heads, scores,
-                                          apply_leaky_relu != 0, negative_slope, out, hs));
+                                          apply_leaky_relu != 0, negative_slope, out, fused, hs));
 }
 
 fg_status fg_gspmm_max_backward(const fg_graph* g, fg_msg_op msg, int32_t num_heads,

@@ -15,7 +15,7 @@ hipError_t launch_gsddmm(const GraphView&, const PlanView*, int64_t, int64_t, co
   return hipErrorNotSupported;
 }
 hipError_t launch_edge_softmax(const GraphView&, const PlanView*, int64_t, const float*, bool, float,
-                               float*, hipStream_t) {
+                               float*, bool, hipStream_t) {
   return hipErrorNotSupported;
 }
 bool gsddmm_softmax_fused(int64_t, int64_t, const float*, const float*) { return false; }

@@ -360,3 +360,40 @@ def test_repeated_edges_order(d):
         np.testing.assert_array_equal(host(fg.gspmm(G, x, w, msg="src_mul_edge", plan=plan)), y)
         fg.gspmm_noalloc(G, x, out, edge=w, msg="src_mul_edge", plan=plan)
         np.testing.assert_array_equal(host(out), y)
+
+
+@pytest.mark.parametrize("deg,long_row,segment,two_pass", [(100, 3000, 1000, True),
+                                                           (40, 1000, 0, False)])
+def test_scores_and_softmax_small_weights(deg, long_row, segment, two_pass):
+    """Weights of e^-80 to 1 to a few units in the last place, whichever route
+    the call takes: as two operators on plans of 56 edges an item and more, and
+    for rows that a plan's shorter pieces cut.  Integer scores, so that only the
+    exponentials, the sum and its reciprocal round: expf to one ulp (2 units of
+    2^-24), the reciprocal and the product half an ulp each, and the sum half an
+    ulp an addition (two a lane and six over the lanes for 128 edges, 24 and a
+    merge of three for the long row)."""
+    rng = np.random.default_rng(deg)
+    n, m, d = 200, 81, 128
+    counts = np.full(n, deg)
+    counts[7] = long_row
+    dst = np.repeat(np.arange(n), counts).astype(np.int64)
+    src = rng.integers(0, m, dst.size).astype(np.int64)
+    src[np.r_[0, np.cumsum(counts)[:-1]]] = 0  # a score of 0 in every row
+    csr = synth.coo_to_csr(dst, src, n, m)
+    x = np.zeros((m, d), np.float32)
+    x[:, 3] = -np.arange(m)
+    xd = np.ones((n, d), np.float32)
+    G = fg.Graph.from_csr(csr)
+    plan = fg.Plan(G, d, segment_edges=segment)
+    info = plan.info()
+    assert info["num_split_rows"] == 1
+    assert (csr.nnz >= 56 * info["num_segments"]) == two_pass
+    s, a = fg.gsddmm_edge_softmax(G, dev(x), dev(xd), leaky=False, plan=plan)
+    np.testing.assert_array_equal(host(s), -csr.indices.astype(np.float32))
+    e = np.exp(-csr.indices.astype(np.float64))
+    rows = synth.csr_rows(csr)
+    ref = e / np.bincount(rows, e, n)[rows]
+    err = np.abs(host(a) / ref - 1)
+    short = rows != 7
+    assert err[short].max() <= 16 * 2.0**-24, err[short].max()
+    assert err[~short].max() <= 36 * 2.0**-24, err[~short].max()
