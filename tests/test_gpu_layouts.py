@@ -397,3 +397,22 @@ def test_scores_and_softmax_small_weights(deg, long_row, segment, two_pass):
     short = rows != 7
     assert err[short].max() <= 16 * 2.0**-24, err[short].max()
     assert err[~short].max() <= 36 * 2.0**-24, err[~short].max()
+
+
+@pytest.mark.parametrize("heads,dh", [(1, 16), (4, 32), (2, 128)])
+def test_attention_split_rows_divide(heads, dh):
+    """A split row's output is its weighted sum over its exponential sum, in one
+    rounding: with equal scores and equal features both sums are exact and the
+    quotient is the feature itself (49 times the rounded 1/49 is not 1)."""
+    n = 80
+    counts = np.arange(n) * 7 + 41  # 49, 98, 196, ... among them
+    dst = np.repeat(np.arange(n), counts).astype(np.int64)
+    csr = synth.coo_to_csr(dst, np.arange(dst.size) % 30, n, 30)
+    G = fg.Graph.from_csr(csr)
+    plan = fg.Plan(G, heads * dh, segment_edges=20, item_order=1)
+    assert plan.info()["num_split_rows"] == n
+    x = dev(np.full((30, heads, dh), 3.0, np.float32))
+    xd = dev(np.zeros((n, heads, dh), np.float32))
+    say("attention over equal scores, H=%d dh=%d" % (heads, dh))
+    np.testing.assert_array_equal(host(fg.gat_aggregate(G, x, xd, plan=plan)),
+                                  np.full((n, heads, dh), 3.0, np.float32))
