@@ -179,6 +179,14 @@ def _width(t: torch.Tensor) -> int:
     return math.prod(t.shape[1:])
 
 
+def _new(like: torch.Tensor, shape) -> torch.Tensor:
+    """An uninitialised float32 tensor on like's device; a plain one also where
+    like is of a subclass (whose new_empty would give the subclass)."""
+    if type(like) is torch.Tensor:
+        return like.new_empty(shape)  # (less host work than torch.empty)
+    return torch.empty(shape, dtype=torch.float32, device=like.device)
+
+
 def _dev_tensor(t: torch.Tensor, dtype: torch.dtype, name: str) -> torch.Tensor:
     if not isinstance(t, torch.Tensor):
         raise TypeError("%s must be a torch.Tensor" % name)
@@ -447,7 +455,7 @@ def gspmm(g: Graph, x: torch.Tensor, edge: Optional[torch.Tensor] = None, msg: s
     elif edge is not None:
         raise ValueError("copy_src takes no edge values")
     shape = (g.num_rows,) + tuple(x.shape[1:])
-    out = x.new_empty(shape) if out is None else _dev_tensor(out, torch.float32, "out")
+    out = _new(x, shape) if out is None else _dev_tensor(out, torch.float32, "out")
     if out.numel() != g.num_rows * F:
         raise ValueError("out has the wrong size")
     if reduce == "max":
@@ -529,7 +537,7 @@ def gsddmm(g: Graph, x_src: torch.Tensor, x_dst: Optional[torch.Tensor] = None, 
     if F % heads:
         raise ValueError("feature width not divisible by heads")
     shape = (g.nnz_total, heads) if (heads > 1 or x_src.dim() == 3) else (g.nnz_total,)
-    out = x_src.new_empty(shape) if out is None else _dev_tensor(out, torch.float32, "out")
+    out = _new(x_src, shape) if out is None else _dev_tensor(out, torch.float32, "out")
     if out.numel() != g.nnz_total * heads:
         raise ValueError("out has the wrong size")
     st = _lib.fg_gsddmm(g._ref, EDGE_OPS[op], heads, F // heads, _ptr(x_src),
@@ -607,7 +615,7 @@ def gat_aggregate(g: Graph, x_src: torch.Tensor, x_dst: Optional[torch.Tensor] =
     if F % heads:
         raise ValueError("feature width not divisible by heads")
     shape = (g.num_rows,) + tuple(x_src.shape[1:])
-    out = x_src.new_empty(shape) if out is None else _dev_tensor(out, torch.float32, "out")
+    out = _new(x_src, shape) if out is None else _dev_tensor(out, torch.float32, "out")
     if out.numel() != g.num_rows * F:
         raise ValueError("out has the wrong size")
     st = _lib.fg_gat_aggregate(g._ref, heads, F // heads, _ptr(x_src), _ptr(x_dst),

@@ -2,6 +2,7 @@
 against the oracle."""
 import numpy as np
 import pytest
+import torch
 
 import synth
 import test_gpu_parity
@@ -416,3 +417,15 @@ def test_attention_split_rows_divide(heads, dh):
     say("attention over equal scores, H=%d dh=%d" % (heads, dh))
     np.testing.assert_array_equal(host(fg.gat_aggregate(G, x, xd, plan=plan)),
                                   np.full((n, heads, dh), 3.0, np.float32))
+
+
+def test_results_are_plain_tensors():
+    """Inputs of a tensor subclass give plain tensors."""
+    class Sub(torch.Tensor):
+        pass
+
+    csr = _graph(1, 20, 20, 0, 9)
+    G = fg.Graph.from_csr(csr)
+    x = dev(np.ones((20, 4), np.float32)).as_subclass(Sub)
+    for y in (fg.gspmm(G, x), fg.gsddmm(G, x, x), fg.gat_aggregate(G, x, x)):
+        assert type(y) is torch.Tensor
