@@ -247,7 +247,7 @@ fg_status fg_schedule_host(const int32_t* indptr_host, const int32_t* indices_ho
  * indptr_host / indices_host: optional HOST copies of g->indptr / g->indices
  * (without them the plan copies what it needs from the device: indptr, the
  * indices when source slabs may apply, else 64 windows of them for the item
- * order).  opt may be NULL.  Validates indptr, and the indices whenever it
+ * order and fg_plan_merges_repeats).  opt may be NULL.  Validates indptr, and the indices whenever it
  * holds them all on the host (FG_ERR_INVALID_ARG), allocates device memory,
  * synchronises `stream`.  The plan is bound to g->indptr, num_rows and
  * nnz: calls with another graph are rejected with FG_ERR_INVALID_ARG; it
@@ -259,6 +259,13 @@ fg_status fg_plan_create(const fg_graph* g, const int32_t* indptr_host,
                          const fg_plan_options* opt, fg_plan** out, void* stream);
 fg_status fg_plan_destroy(fg_plan* plan);
 fg_status fg_plan_get_info(const fg_plan* plan, fg_plan_info* info);
+
+/* 1 if fg_gspmm and fg_gsddmm may merge the copies of repeated edges on this
+ * plan, else 0: at least a tenth of the edges in 64 windows of 32 rows (graphs
+ * of 64 rows or more) repeat the stored edge before them.  Sums are then
+ * rounded differently (copies' weights are added first), in an order that the
+ * plan and the stored edges fix. */
+fg_status fg_plan_merges_repeats(const fg_plan* plan, int32_t* out);
 
 /* Checksum of a HOST indptr array [num_rows + 1]: 64-bit FNV-1a over the
  * little-endian bytes of its int32 entries (offset basis 14695981039346656037,

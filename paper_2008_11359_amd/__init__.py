@@ -116,6 +116,8 @@ def _load():
     lib.fg_plan_destroy.argtypes = [vp]
     lib.fg_plan_get_info.restype = ctypes.c_int
     lib.fg_plan_get_info.argtypes = [vp, ctypes.POINTER(_PlanInfo)]
+    lib.fg_plan_merges_repeats.restype = ctypes.c_int
+    lib.fg_plan_merges_repeats.argtypes = [vp, ctypes.POINTER(i32)]
     lib.fg_indptr_checksum.restype = ctypes.c_int
     lib.fg_indptr_checksum.argtypes = [vp, i64, ctypes.POINTER(ctypes.c_uint64)]
     lib.fg_plan_validate.restype = ctypes.c_int
@@ -348,7 +350,11 @@ class Plan:
     def info(self) -> dict:
         inf = _PlanInfo()
         _check(_lib.fg_plan_get_info(self.handle, ctypes.byref(inf)), "fg_plan_get_info")
-        return {k: getattr(inf, k) for k, _ in _PlanInfo._fields_}
+        merges = ctypes.c_int32()
+        _check(_lib.fg_plan_merges_repeats(self.handle, ctypes.byref(merges)),
+               "fg_plan_merges_repeats")
+        return {**{k: getattr(inf, k) for k, _ in _PlanInfo._fields_},
+                "merges_repeats": merges.value}
 
     def close(self) -> None:
         if self._h is not None:

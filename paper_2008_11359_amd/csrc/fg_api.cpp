@@ -978,7 +978,7 @@ fg_status fg_plan_create(const fg_graph* g, const int32_t* indptr_host,
       for (const auto& w : wins) win_ix.emplace_back(ix + ip[w.first], ix + ip[w.second]);
       repeats = repeat_share(ip, wins, win_ix) >= kRepeatShare;
       settle_options(o, ip, ix, g->num_rows, g->num_cols, max_width, -1);
-    } else if (o.order == kOrderAuto) {  // sample windows of the device indices
+    } else {  // sample windows of the device indices
       const auto wins = order_windows(ip, g->num_rows);
       std::vector<std::vector<int32_t>> win_ix;
       for (const auto& w : wins) {
@@ -990,8 +990,10 @@ fg_status fg_plan_create(const fg_graph* g, const int32_t* indptr_host,
           return FG_ERR_HIP;
       }
       if (!wins.empty() && hipStreamSynchronize(hs) != hipSuccess) return FG_ERR_HIP;
-      o.order = ids_share_sources(ip, wins, win_ix) ? kOrderById : kOrderByLength;
-      o.band_auto = o.order == kOrderByLength;
+      if (o.order == kOrderAuto) {
+        o.order = ids_share_sources(ip, wins, win_ix) ? kOrderById : kOrderByLength;
+        o.band_auto = o.order == kOrderByLength;
+      }
       repeats = repeat_share(ip, wins, win_ix) >= kRepeatShare;
     }
   } catch (const std::bad_alloc&) {
@@ -1108,6 +1110,12 @@ fg_status fg_plan_create(const fg_graph* g, const int32_t* indptr_host,
     return FG_ERR_HIP;
   }
   *out = p;
+  return FG_OK;
+}
+
+fg_status fg_plan_merges_repeats(const fg_plan* plan, int32_t* out) {
+  if (!plan || !out) return FG_ERR_INVALID_ARG;
+  *out = plan->gather.repeats ? 1 : 0;
   return FG_OK;
 }
 

@@ -429,3 +429,21 @@ def test_results_are_plain_tensors():
     x = dev(np.ones((20, 4), np.float32)).as_subclass(Sub)
     for y in (fg.gspmm(G, x), fg.gsddmm(G, x, x), fg.gat_aggregate(G, x, x)):
         assert type(y) is torch.Tensor
+
+
+@pytest.mark.parametrize("share", [0.0, 0.5])
+def test_repeats_hint(share):
+    """Whether a plan merges repeated edges depends on the graph alone: not on
+    the item order asked for, nor on host copies of the indices."""
+    rng = np.random.default_rng(3)
+    n = 100
+    src = np.stack([rng.permutation(400)[:60] for _ in range(n)]).astype(np.int64)
+    src = np.concatenate([src, src[:, :int(60 * share)]], axis=1)
+    csr = synth.coo_to_csr(np.repeat(np.arange(n), src.shape[1]).astype(np.int64), src.reshape(-1),
+                           n, 400)
+    G = fg.Graph.from_csr(csr)
+    D = fg.Graph(n, 400, G.indptr, G.indices)  # no host copies
+    assert G.indices_host is not None and D.indices_host is None
+    for g in (G, D):
+        for order in (0, 1, 2, 3):
+            assert fg.Plan(g, 32, item_order=order).info()["merges_repeats"] == (share > 0)
