@@ -447,3 +447,28 @@ def test_repeats_hint(share):
     for g in (G, D):
         for order in (0, 1, 2, 3):
             assert fg.Plan(g, 32, item_order=order).info()["merges_repeats"] == (share > 0)
+
+
+@pytest.mark.parametrize("heads,dh", [(1, 128), (4, 32), (8, 4)])
+@pytest.mark.parametrize("segment", [0, 40])
+def test_attention_nan_and_infinite_scores(heads, dh, segment):
+    """A NaN or an infinite score makes its row's head NaN and leaves the other
+    rows and heads alone, in whole rows and in split ones, wherever it stands."""
+    rng = np.random.default_rng(dh)
+    n, m = 70, 300
+    src = np.stack([np.sort(rng.permutation(m)[:90]) for _ in range(n)]).astype(np.int64)
+    csr = synth.coo_to_csr(np.repeat(np.arange(n), 90).astype(np.int64), src.reshape(-1), n, m)
+    G = fg.Graph.from_csr(csr)
+    plan = fg.Plan(G, heads * dh, segment_edges=segment)
+    x = rng.standard_normal((m, heads, dh)).astype(np.float32)
+    xd = (rng.random((n, heads, dh)) + 0.5).astype(np.float32)
+    clean = host(fg.gat_aggregate(G, dev(x), dev(xd), plan=plan))
+    assert np.isfinite(clean).all()
+    x[11, 0, 1], x[200, heads - 1, 2] = np.nan, np.inf
+    y = host(fg.gat_aggregate(G, dev(x), dev(xd), plan=plan))
+    hit = np.zeros((n, heads), bool)
+    hit[:, 0] |= (src == 11).any(1)
+    hit[:, heads - 1] |= (src == 200).any(1)
+    assert hit.any(0)[[0, heads - 1]].all() and not hit.all()
+    assert np.isnan(y[hit]).all()
+    np.testing.assert_array_equal(y[~hit], clean[~hit])
