@@ -222,7 +222,7 @@ def test_repeated_edges(d):
 
     G = fg.Graph.from_csr(csr)
     for segment in (0, 300):
-        check(csr, G, fg.Plan(G, d, segment_edges=segment))
+        check(csr, G, _merging_plan(G, d, segment))
     w = rng.standard_normal((8, d)).astype(np.float32)
     check_mlp(csr, G, rng.standard_normal((m, 8)).astype(np.float32),
               rng.standard_normal((n, 8)).astype(np.float32), w, plan=fg.Plan(G, d))
@@ -242,16 +242,25 @@ def test_repeated_edges(d):
     check(synth.CSR(n, m, csr.indptr, mixed), G, plan)
 
 
+def _merging_plan(G, d, segment):
+    """A plan on which the gather kernels merge repeated edges (the layouts of
+    65 to 128 floats take their wide batches from 112 edges an item on)."""
+    plan = fg.Plan(G, d, segment_edges=segment)
+    info = plan.info()
+    assert info["merges_repeats"] and G.nnz >= 112 * info["num_segments"]
+    return plan
+
+
 def test_repeated_edges_infinities():
     """Copies of an infinite or NaN source stay what repeated adds give."""
-    n, m, d = 40, 20, 128
+    n, m, d = 128, 20, 128
     rng = np.random.default_rng(0)
     dst = np.repeat(np.arange(n), 300).astype(np.int64)
     csr = synth.coo_to_csr(dst, rng.integers(0, m, dst.size).astype(np.int64), n, m)
     x = rng.standard_normal((m, d)).astype(np.float32)
     x[3, 5], x[4, 6], x[5, 7] = np.inf, -np.inf, np.nan
     G = fg.Graph.from_csr(csr)
-    plan = fg.Plan(G, d)
+    plan = _merging_plan(G, d, 300)
     y = host(fg.gspmm(G, dev(x), plan=plan))
     with np.errstate(invalid="ignore"):
         ref = np.zeros((n, d))
@@ -289,7 +298,7 @@ def test_repeated_edges_weights(d, w):
     """Weighted copies of an edge to infinite, NaN, zero and small features: what
     adding them one by one gives, where their weights have two signs, a zero or
     a sum that overflows as where they have one sign."""
-    n, m = 20, 16
+    n, m = 128, 16
     dst = np.repeat(np.arange(n), 512).astype(np.int64)
     csr = synth.coo_to_csr(dst, np.tile(np.repeat(np.arange(m), 32), n).astype(np.int64), n, m)
     assert np.mean(csr.indices[1:] == csr.indices[:-1]) > 0.5
@@ -298,7 +307,7 @@ def test_repeated_edges_weights(d, w):
     ew = np.full(csr.nnz, 0.5, np.float32)
     ew[100:102] = ew[1000:1002] = ew[1535:1537] = ew[130:132] = ew[163:165] = w
     G = fg.Graph.from_csr(csr)
-    y = host(fg.gspmm(G, dev(x), dev(ew), msg="src_mul_edge", plan=fg.Plan(G, d)))
+    y = host(fg.gspmm(G, dev(x), dev(ew), msg="src_mul_edge", plan=_merging_plan(G, d, 512)))
     ref = np.zeros((n, d))
     with np.errstate(invalid="ignore"):
         np.add.at(ref, synth.csr_rows(csr),
@@ -347,13 +356,13 @@ def test_repeated_edges_order(d):
         k, v = _run_sums(csr.indices[256 * r:256 * r + 256], w[256 * r:256 * r + 256])
         want[r, k] = v
     G = fg.Graph.from_csr(csr)
-    plan = fg.Plan(G, d, segment_edges=256)
+    plan = _merging_plan(G, d, 256)
     x, w = dev(np.eye(m, dtype=np.float32)), dev(w)
     for _ in range(3):
         y = host(fg.gspmm(G, x, w, msg="src_mul_edge", plan=plan))
         np.testing.assert_array_equal(y, want)
     # rows in pieces, any features: call to call, and without allocation
-    plan = fg.Plan(G, d, segment_edges=150, item_order=1)
+    plan = _merging_plan(G, d, 150)
     x = dev(rng.standard_normal((m, d)).astype(np.float32))
     y = host(fg.gspmm(G, x, w, msg="src_mul_edge", plan=plan))
     out = dev(np.zeros((n, d), np.float32))
@@ -447,6 +456,23 @@ def test_repeats_hint(share):
     for g in (G, D):
         for order in (0, 1, 2, 3):
             assert fg.Plan(g, 32, item_order=order).info()["merges_repeats"] == (share > 0)
+
+
+@pytest.mark.parametrize("d", [72, 128])
+def test_repeated_edges_subnormal_weights(d):
+    """Copies whose weights are subnormal keep every bit: integers of 2^-149
+    times features of 2^100, with sums below 2^24, are exact."""
+    n, m = 128, 16
+    rng = np.random.default_rng(d)
+    dst = np.repeat(np.arange(n), 256).astype(np.int64)
+    csr = synth.coo_to_csr(dst, rng.integers(0, m, dst.size).astype(np.int64), n, m)
+    k = rng.integers(1, 4096, csr.nnz)
+    G = fg.Graph.from_csr(csr)
+    x = np.full((m, d), 2.0**100, np.float32)
+    y = host(fg.gspmm(G, dev(x), dev(np.ldexp(k.astype(np.float64), -149).astype(np.float32)),
+                      msg="src_mul_edge", plan=_merging_plan(G, d, 256)))
+    want = np.ldexp(np.bincount(synth.csr_rows(csr), k, n), -49)[:, None] * np.ones(d)
+    np.testing.assert_array_equal(y.astype(np.float64), want)
 
 
 @pytest.mark.parametrize("heads,dh", [(1, 128), (4, 32), (8, 4)])
