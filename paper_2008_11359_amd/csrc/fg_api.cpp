@@ -1057,6 +1057,11 @@ fg_status fg_plan_create(const fg_graph* g, const int32_t* indptr_host,
     v->ws_width = ws_width;
     v->repeats = repeats;
   }
+  for (int64_t r = 0; r < g->num_rows; ++r) {
+    const int64_t deg = (int64_t)ip[r + 1] - ip[r];
+    if (deg <= fg::kRegisterRowEdges4) p->plain.register_edges4 += deg;
+    if (deg <= fg::kRegisterRowEdges8) p->plain.register_edges8 += deg;
+  }
   p->workspace_bytes = (int64_t)(wb[0] + wb[1] + wb[2]);
   if (g->edge_ids) {
     p->edge_ids = g->edge_ids;

@@ -271,13 +271,17 @@ def test_repeated_edges_infinities():
     np.testing.assert_allclose(y[fin], ref[fin], rtol=2e-5, atol=2e-4)
 
 
+@pytest.mark.parametrize("more", [0, 40])
 @pytest.mark.parametrize("heads,batches", [(8, 6), (4, 12)])
-def test_score_gradient_row_lengths(heads, batches):
+def test_score_gradient_row_lengths(heads, batches, more):
     """Rows around the longest whose gradients stay in registers (6 batches of
-    64 edges with 8 heads, 12 with 4), and around one batch."""
+    64 edges with 8 heads, 12 with 4), and around one batch; the register form
+    runs where rows that it holds have three quarters of the edges (more)."""
     rng = np.random.default_rng(heads)
     top = 64 * batches
     deg = np.array([0, 1, 63, 64, 65, 128, top - 1, top, top + 1, top + 64, 2 * top, 3])
+    deg = np.concatenate([deg, np.full(more, top)])
+    assert (4 * deg[deg <= top].sum() >= 3 * deg.sum()) == (more > 0)
     n = deg.size
     dst = np.repeat(np.arange(n), deg).astype(np.int64)
     csr = synth.coo_to_csr(dst, rng.integers(0, 50, dst.size).astype(np.int64), n, 50)
