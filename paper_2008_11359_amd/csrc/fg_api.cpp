@@ -68,7 +68,8 @@ constexpr int32_t kDefaultPlainSegmentEdges = 16384;
 //   2.5M,  1 x 64              63 -> 47         69 -> 45      67 -> 60
 // and the softmax and its backward, heads of 400K 8: 114 -> 28 and 95 -> 26,
 // 2.5M 1: 54 -> 25 and 46 -> 35, 10M 8: 394 -> 221 and 562 -> 325.  Graphs of
-// 6.3M edges (67M: softmax) or more keep the defaults above.
+// 6.3M edges (67M: softmax) or more keep the defaults above, and so do graphs
+// whose rows such pieces would cut to no use (see piece_cost).
 constexpr int64_t kItemsOfAGraph = 4096;
 constexpr int64_t kMinPieceFloats = 16384;
 constexpr int64_t kMinPieceEdgesGather = 128, kMinPieceEdgesPlain = 512;
@@ -310,7 +311,20 @@ constexpr int64_t kEdgeSlabs = 16;
 constexpr int64_t kEdgePieceEdges = 4;
 constexpr int64_t kInfinityCacheBytes = int64_t(256) << 20;
 
+// What pieces of S edges cost, in edges that a wavefront walks while the others
+// do: a chip's share of the edges (two wavefronts a SIMD) or the longest piece,
+// plus kSlotEdges for every partial result, written and read once more by the
+// merge, and kMergeEdges for that launch.  From uniform graphs cut in 1 .. 16
+// pieces a row (us, sum of 128 floats; 20 edges a microsecond): 250 rows of 1600
+// edges: 47 whole, 29 in 2, 17 in 4, 13 in 8; 1000 of 400: 15, 16, 22; 2000 of
+// 400: 19, 29; 4000 of 400: 39, 61; 8000 of 300: 72, 102.  Default pieces of
+// 1/4096 of the edges cut nearly all rows of the last three.
+constexpr int64_t kShareItems = 2048, kSlotEdges = 70, kMergeEdges = 60;
+// Longer pieces than that default only if they save this share of its cost.
+constexpr double kPieceGain = 0.1;
+
 struct Options {
+  bool auto_gather, auto_plain;  // piece lengths chosen here, not by the caller
   int32_t S, cap, slab, min_deg;  // slab 0: no source partitioning
   int32_t S_whole;                // S of partitioned schedules, and the one that decides whether
                                   // the automatic order bands: given, else kDefaultSegmentEdges
@@ -440,6 +454,42 @@ int64_t row_pieces(int64_t deg, int32_t S, int64_t cap, int64_t band_rows) {
   const int64_t kmin = std::min<int64_t>(kXcds, cap);
   if (band_rows >= 0 && deg > band_rows && k < kmin) k = std::min(kmin, deg);
   return k;
+}
+
+// See kSlotEdges.
+int64_t piece_cost(const int32_t* ip, int64_t num_rows, int32_t S, int64_t cap, int64_t band_rows,
+                   int64_t* slots) {
+  int64_t n = 0, longest = 0;
+  for (int64_t r = 0; r < num_rows; ++r) {
+    const int64_t deg = (int64_t)ip[r + 1] - ip[r];
+    const int64_t k = row_pieces(deg, S, cap, band_rows);
+    if (k >= 2) n += k;
+    longest = std::max(longest, (deg + k - 1) / k);
+  }
+  *slots = n;
+  return std::max(ip[num_rows] / kShareItems, longest) + n * kSlotEdges / kShareItems +
+         (n > 0 ? kMergeEdges : 0);
+}
+
+// Default pieces of a schedule: S, or the cheapest of 2S, 4S, .. top where it
+// costs kPieceGain less.
+int32_t settle_default(const int32_t* ip, int64_t num_rows, int32_t S, int32_t top, int64_t cap,
+                       int64_t band_rows) {
+  int64_t slots = 0;
+  int64_t least = piece_cost(ip, num_rows, S, cap, band_rows, &slots);
+  if (slots == 0) return S;
+  least = (int64_t)((1.0 - kPieceGain) * (double)least);
+  int32_t best = S;
+  for (int64_t t = S; t < top;) {
+    t = std::min<int64_t>(2 * t, top);
+    const int64_t c = piece_cost(ip, num_rows, (int32_t)t, cap, band_rows, &slots);
+    if (c < least) {
+      least = c;
+      best = (int32_t)t;
+    }
+    if (slots == 0) break;  // longer pieces cut nothing either
+  }
+  return best;
 }
 
 // The gather schedule's segment length: o.S, doubled while its partial
@@ -691,6 +741,7 @@ fg_status read_options(const fg_plan_options* opt, int64_t nnz, int64_t num_cols
                        kDefaultSegmentEdges);
   o->S_plain = default_piece(nnz, kMinPieceEdgesPlain, kDefaultPlainSegmentEdges);
   o->S_whole = kDefaultSegmentEdges;
+  o->auto_gather = o->auto_plain = true;
   o->max_width = max_width;
   o->cap = kDefaultMaxRowSegments;
   o->slab = 0;
@@ -715,9 +766,11 @@ fg_status read_options(const fg_plan_options* opt, int64_t nnz, int64_t num_cols
     if (opt->partition_min_degree < 0) return FG_ERR_INVALID_ARG;
     if (opt->source_slab_rows < kSlabsOff) return FG_ERR_INVALID_ARG;
     if (opt->segment_edges) o->S = o->S_plain = o->S_whole = opt->segment_edges;
+    if (opt->segment_edges) o->auto_gather = o->auto_plain = false;
     if (opt->softmax_segment_edges < 0 || opt->softmax_segment_edges > kMaxSegmentEdges)
       return FG_ERR_INVALID_ARG;
     if (opt->softmax_segment_edges) o->S_plain = opt->softmax_segment_edges;
+    if (opt->softmax_segment_edges) o->auto_plain = false;
     if (opt->band_row_edges < -1 || opt->band_row_edges > kMaxSegmentEdges)
       return FG_ERR_INVALID_ARG;
     if (opt->band_row_edges) o->band_rows = opt->band_row_edges;
@@ -751,7 +804,8 @@ fg_status make_schedules(const int32_t* ip, const int32_t* ix, int64_t num_rows,
                          Schedule* edge = nullptr) {
   try {
     Options op = o;
-    op.S = o.S_plain;
+    op.S = o.auto_plain ? settle_default(ip, num_rows, o.S_plain, kDefaultPlainSegmentEdges, o.cap, -1)
+                        : o.S_plain;
     build_plain(ip, num_rows, op, plain);
     Options og = o;
     og.S = o.S_whole;
@@ -764,8 +818,9 @@ fg_status make_schedules(const int32_t* ip, const int32_t* ix, int64_t num_rows,
         band = std::min<int64_t>((max_deg + o.S_whole - 1) / o.S_whole, o.cap) >= kXcds;
       }
       const int64_t band_rows = band ? o.band_rows : -1;
-      og.S = settle_segment(ip, num_rows, o, band_rows);
-      if (o.S_plain == og.S && band_rows < 0) {
+      og.S = o.auto_gather ? settle_default(ip, num_rows, o.S, o.S_whole, o.cap, band_rows) : o.S;
+      og.S = settle_segment(ip, num_rows, og, band_rows);
+      if (op.S == og.S && band_rows < 0) {
         gather = plain;
       } else {
         gather = Schedule();
@@ -1057,8 +1112,10 @@ fg_status fg_plan_create(const fg_graph* g, const int32_t* indptr_host,
     v->ws_width = ws_width;
     v->repeats = repeats;
   }
+  p->plain.longest_row = o.auto_plain ? 0 : INT64_MAX;
   for (int64_t r = 0; r < g->num_rows; ++r) {
     const int64_t deg = (int64_t)ip[r + 1] - ip[r];
+    p->plain.longest_row = std::max(p->plain.longest_row, deg);
     if (deg <= fg::kRegisterRowEdges4) p->plain.register_edges4 += deg;
     if (deg <= fg::kRegisterRowEdges8) p->plain.register_edges8 += deg;
   }

@@ -439,6 +439,16 @@ __device__ __forceinline__ Item load_item(const Seg* segs, const int32_t* indptr
   return it;
 }
 
+// For launches that take a plan's cut rows whole: the first piece becomes the
+// row, the others (false) have nothing to do.
+__device__ __forceinline__ bool take_whole_row(Item& it, const int32_t* indptr) {
+  if (it.slot < 0) return true;
+  if (it.b != indptr[it.row]) return false;
+  it.e = indptr[it.row + 1];
+  it.slot = -1;
+  return true;
+}
+
 inline int ilog2_ceil(int64_t q) {
   int l = 0;
   while ((int64_t(1) << l) < q) ++l;

@@ -771,3 +771,19 @@ def test_sddmm_schedule_needs_long_rows(deg, own):
     gather = fg.schedule_host(indptr, which="gather", **kw)[0]
     sddmm = fg.schedule_host(indptr, which="sddmm", **kw)[0]
     assert (len(sddmm) != len(gather)) == own
+
+
+@pytest.mark.parametrize("n,deg", [(2000, 400), (3000, 800), (4000, 400), (2000, 1500)])
+def test_balanced_rows_stay_whole(n, deg):
+    """Where a few thousand rows of about equal length share the edges, pieces
+    of 1/4096 of them would cut nearly every row, and the merge costs more than
+    they give; one long row among them is still cut, and so are few rows."""
+    ptr = (np.arange(n + 1) * deg).astype(np.int32)
+    for which in ("gather", "plain"):
+        assert fg.schedule_host(ptr, max_width=128, which=which)[1:] == (0, 0)
+    ptr[n // 2:] += 40 * deg
+    for which in ("gather", "plain"):
+        segs, split, slots = fg.schedule_host(ptr, max_width=128, which=which)
+        assert split >= 1 and (segs[:, 2] - segs[:, 1]).max() <= 10 * deg
+    few = (np.arange(251) * 1600).astype(np.int32)
+    assert fg.schedule_host(few, max_width=128)[1] == 250

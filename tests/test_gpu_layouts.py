@@ -6,7 +6,8 @@ import torch
 
 import synth
 import test_gpu_parity
-from test_gpu_parity import (check_dense_matmul, check_mlp, check_sddmm,
+from test_gpu_parity import (check_dense_matmul, check_mlp, check_sddmm, check_softmax,
+                             check_softmax_backward,
                              check_sddmm_softmax, check_sddmm_softmax_backward, check_spmm, dev, host,
                              say)
 
@@ -502,3 +503,38 @@ def test_attention_nan_and_infinite_scores(heads, dh, segment):
     assert hit.any(0)[[0, heads - 1]].all() and not hit.all()
     assert np.isnan(y[hit]).all()
     np.testing.assert_array_equal(y[~hit], clean[~hit])
+
+
+@pytest.mark.parametrize("heads", [1, 2, 4, 5, 8])
+def test_softmax_cut_rows_taken_whole(heads):
+    """Plans that cut rows by themselves: with few values a row the softmax and
+    its backward take the rows whole (700 edges with up to 5 heads), with more
+    in pieces; the score gradient runs as one pass where no row outlasts the
+    rest (nnz / 2048 edges), else as two operators.  With edge ids as well."""
+    rng = np.random.default_rng(heads)
+    for n, rest in ((300, 20), (15000, 96)):
+        deg = rng.integers(rest // 2, rest + rest // 2, n)
+        deg[5], deg[n - 2], deg[9] = 700, 513, 0
+        dst = np.repeat(np.arange(n), deg).astype(np.int64)
+        csr = synth.coo_to_csr(dst, rng.integers(0, 500, dst.size).astype(np.int64), n, 500)
+        G = fg.Graph.from_csr(csr)
+        plan = fg.Plan(G, heads * 4)
+        assert plan.info()["plain_slots"] >= 2
+        rows = np.r_[0:12, n // 2, n - 3:n]
+        s = (3 * rng.standard_normal((csr.nnz, heads))).astype(np.float32)
+        go = rng.standard_normal((csr.nnz, heads)).astype(np.float32)
+        for leaky in (True, False):
+            check_softmax(csr, G, s, rows=rows, plan=plan, heads=heads, leaky=leaky)
+            check_softmax_backward(csr, G, s, go, rows=rows, plan=plan, heads=heads, leaky=leaky)
+            if heads > 1:
+                x = rng.integers(-3, 4, (500, heads, 4)).astype(np.float32)
+                dy = rng.integers(-3, 4, (n, heads, 4)).astype(np.float32)
+                check_sddmm_softmax_backward(csr, G, x, dy, s, plan=plan, leaky=leaky, rows=rows)
+    csc = synth.csr_to_csc(csr)
+    deg = csc.degrees()
+    Gt = fg.Graph.from_csr(csc, nnz_total=csr.nnz)
+    plan = fg.Plan(Gt, heads * 4)
+    assert plan.info()["plain_slots"] >= 2 and deg.max() > 2000
+    rows = np.r_[0:5, deg.argmax()]
+    check_softmax(csc, Gt, s, rows=rows, plan=plan, heads=heads, nnz_total=csr.nnz)
+    check_softmax_backward(csc, Gt, s, go, rows=rows, plan=plan, heads=heads, nnz_total=csr.nnz)
