@@ -467,9 +467,11 @@ fg_status fg_edge_softmax_backward(const fg_graph* g, int32_t num_heads, const f
  *            apply_leaky_relu
  * grad_scores [nnz_total, H]; entries of edges of g are written.  It must not
  *            overlap any input.
- * One fused pass when 2 <= H <= 16, head_dim is 4, 8, 16, 32 or 64, H * head_dim
- * <= 256, the feature arrays are 16-byte aligned and the plan (if any) cuts
- * no row of its softmax schedule; otherwise the same results through
+ * One fused pass when edge ids are positional, H is 2, or 4, 8 or 16 with all
+ * arrays 16-byte aligned, head_dim is 4, 8, 16, 32 or 64, H * head_dim <= 256,
+ * the feature arrays are 16-byte aligned and the plan (if any) cuts no row of
+ * its softmax schedule, or cuts rows by its own defaults of which none has
+ * more than nnz / 2048 edges; otherwise the same results through
  * fg_gsddmm into grad_scores followed by fg_edge_softmax_backward in place.
  * Sums are fp32 in a fixed order for a given plan (deterministic).
  * ------------------------------------------------------------------------- */

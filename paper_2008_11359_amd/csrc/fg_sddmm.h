@@ -24,7 +24,6 @@ struct SddmmParams {
   int32_t out_vec4;  // output rows of H values are 16-byte aligned float4s
   int32_t repeats;  // the graph repeats many edges (DUP kernels)
   int32_t heads_per_pass;  // heads per blockIdx.y (headed kernel)
-  int32_t whole;  // take the plan's cut rows whole (score gradient only)
 };
 
 // One translation unit each (they build in parallel): single-head SDDMM for
