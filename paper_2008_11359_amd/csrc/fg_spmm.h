@@ -30,7 +30,7 @@ struct SpmmParams {
 
 // One translation unit each (they build in parallel): the float4 kernels of
 // the sum and the max reducer, for 16-byte aligned rows and for any others of
-// at least 4 floats (ragged; also edge values of more than kTabHeads heads).
+// at least 4 floats (ragged).
 // avg: the items' average edge count.
 void spmm_sum(const SpmmParams& prm, bool mul, bool seg, int64_t avg, hipStream_t st);
 void spmm_max(const SpmmParams& prm, bool mul, bool seg, int64_t avg, hipStream_t st);
@@ -744,20 +744,34 @@ void spmm_fast_dispatch(const SpmmParams& prm, bool mul, bool seg, int64_t avg, 
       return;
     }
   }
-  if (Q <= 4) go(SpmmLayout<4, 1, 4, RAG>{}, 1);
-  else if (Q <= 8) go(SpmmLayout<8, 1, 8, RAG>{}, 1);
-  else if (Q <= 16) go(SpmmLayout<16, 1, 8, RAG>{}, 1);
-  else if (Q <= 32) go(SpmmLayout<32, 1, 8, RAG>{}, 1);
-  else if (Q <= 64) go(SpmmLayout<64, 1, 8, RAG>{}, 1);
-  // three float4 a lane where two or four would leave over a quarter of the
-  // lanes idle (10M power-law edges, max: 300 floats 754 -> 725 us, 602 2253 ->
-  // 1777; weighted sum 701 -> 653, 1585 -> 1478; uniform edges, bound by lines
-  // rather than lanes, equal).  16 x 3 for 130-192 floats and 8 x 3 for 66-96
-  // are slower on short rows and equal on long ones.
-  else if (Q <= 96) go(SpmmLayout<32, 3, 4, RAG>{}, 1);
-  else if (Q <= 128) go(SpmmLayout<64, 2, 4, RAG>{}, 1);
-  else if (Q <= 192) go(SpmmLayout<64, 3, 2, RAG>{}, 1);
-  else go(SpmmLayout<64, 4, 2, RAG>{}, (Q + 255) / 256);
+  // the aligned rows' layouts, also with a weight load per float4 and step for
+  // more heads than the table holds
+  auto all = [&](auto many_tag) {
+    constexpr bool MANY = decltype(many_tag)::value;
+    if constexpr (!MANY) {  // (17 heads of 4 features take 17 float4s)
+      if (Q <= 4) return go(SpmmLayout<4, 1, 4, RAG>{}, 1);
+      if (Q <= 8) return go(SpmmLayout<8, 1, 8, RAG>{}, 1);
+      if (Q <= 16) return go(SpmmLayout<16, 1, 8, RAG>{}, 1);
+    }
+    if (Q <= 32) go(SpmmLayout<32, 1, 8, RAG, MANY>{}, 1);
+    else if (Q <= 64) go(SpmmLayout<64, 1, 8, RAG, MANY>{}, 1);
+    // three float4 a lane where two or four would leave over a quarter of the
+    // lanes idle (10M power-law edges, max: 300 floats 754 -> 725 us, 602 2253 ->
+    // 1777; weighted sum 701 -> 653, 1585 -> 1478; uniform edges, bound by lines
+    // rather than lanes, equal).  16 x 3 for 130-192 floats and 8 x 3 for 66-96
+    // are slower on short rows and equal on long ones.
+    else if (Q <= 96) go(SpmmLayout<32, 3, 4, RAG, MANY>{}, 1);
+    else if (Q <= 128) go(SpmmLayout<64, 2, 4, RAG, MANY>{}, 1);
+    else if (Q <= 192) go(SpmmLayout<64, 3, 2, RAG, MANY>{}, 1);
+    else go(SpmmLayout<64, 4, 2, RAG, MANY>{}, (Q + 255) / 256);
+  };
+  if constexpr (!RAG) {
+    if (mul && prm.H > kTabHeads) {
+      all(BoolTag<true>{});
+      return;
+    }
+  }
+  all(BoolTag<false>{});
 }
 
 }  // namespace
