@@ -368,6 +368,10 @@ void sddmm_fast_dispatch(const SddmmParams& prm, bool seg, int64_t avg, hipStrea
 template <int S, bool RAG>
 void sddmm_headed_go(SddmmParams prm, bool seg, hipStream_t st) {
   prm.heads_per_pass = std::min<int32_t>(std::min(kWave / S, kTabHeads), prm.H);
+  if (!prm.out_vec4) {  // equal passes (33 heads: 11 each, not 16, 16 and 1)
+    const int32_t passes = (prm.H + prm.heads_per_pass - 1) / prm.heads_per_pass;
+    prm.heads_per_pass = (prm.H + passes - 1) / passes;
+  }
   prm.logG = ilog2_ceil((int64_t)prm.heads_per_pass * S);
   const dim3 grid =
       grid_for(prm.n_items, (prm.H + prm.heads_per_pass - 1) / prm.heads_per_pass);

@@ -33,13 +33,13 @@ def _graph(seed, n, m, lo, hi):
     return synth.coo_to_csr(dst, rng.integers(0, m, size=dst.size).astype(np.int64), n, m)
 
 
-@pytest.mark.parametrize("d", [4, 5, 7, 17, 31, 33, 41, 63, 65, 126, 129, 255, 257, 300, 383, 385,
+@pytest.mark.parametrize("d", [4, 5, 7, 15, 17, 31, 33, 66, 101, 41, 63, 65, 126, 129, 255, 257, 300, 383, 385,
                                511, 513, 767, 768, 769, 1023, 1025, 2049])
 def test_ragged_rows(d):
     """Widths around every layout's edge, most of them no multiple of 4, with
     64-edge and 256-edge batches, whole and split rows."""
     rng = np.random.default_rng(d)
-    for lo, hi, segment in ((0, 40, 0), (130, 420, 0), (130, 420, 100)):
+    for lo, hi, segment in ((0, 5, 0), (0, 40, 0), (130, 420, 0), (130, 420, 100)):
         csr = _graph(d + lo, 40, 90, lo, hi)
         G = fg.Graph.from_csr(csr)
         x = rng.standard_normal((csr.num_cols, d)).astype(np.float32)
@@ -53,30 +53,33 @@ def test_ragged_rows(d):
             check_sddmm(csr, G, x, xd, plan=plan)
 
 
-@pytest.mark.parametrize("heads,dh", [(2, 3), (3, 5), (8, 6), (16, 10), (17, 3), (20, 4), (40, 7)])
+@pytest.mark.parametrize("heads,dh", [(2, 3), (3, 5), (8, 6), (16, 10), (17, 3), (20, 4), (40, 7),
+                                      (33, 8), (2, 129), (24, 30)])
 def test_ragged_heads(heads, dh):
     """Heads that straddle a lane's four floats, up to and above the heads
     whose weights a wavefront stages in LDS."""
-    csr = _graph(heads, 60, 50, 0, 90)
-    G = fg.Graph.from_csr(csr)
-    rng = np.random.default_rng(dh)
-    x = rng.standard_normal((csr.num_cols, heads, dh)).astype(np.float32)
-    w = rng.standard_normal((csr.nnz, heads)).astype(np.float32)
-    for plan in (None, fg.Plan(G, heads * dh, segment_edges=30)):
-        for reduce in ("sum", "max"):
-            check_spmm(csr, G, x, plan=plan, edge=w, heads=heads, reduce=reduce)
+    for lo, hi, segment in ((0, 90, 30), (100, 300, 90)):  # scalar lanes; float4 lanes
+        csr = _graph(heads, 60, 50, lo, hi)
+        G = fg.Graph.from_csr(csr)
+        rng = np.random.default_rng(dh)
+        x = rng.standard_normal((csr.num_cols, heads, dh)).astype(np.float32)
+        w = rng.standard_normal((csr.nnz, heads)).astype(np.float32)
+        for plan in (None, fg.Plan(G, heads * dh, segment_edges=segment)):
+            for reduce in ("sum", "max"):
+                check_spmm(csr, G, x, plan=plan, edge=w, heads=heads, reduce=reduce)
 
 
 def test_ragged_mlp():
     rng = np.random.default_rng(3)
-    csr = _graph(3, 50, 70, 0, 300)
-    G = fg.Graph.from_csr(csr)
-    xs = rng.standard_normal((csr.num_cols, 8)).astype(np.float32)
-    xd = rng.standard_normal((csr.num_rows, 8)).astype(np.float32)
-    for d_out in (5, 37, 130):
-        w = rng.standard_normal((8, d_out)).astype(np.float32)
-        for plan in (None, fg.Plan(G, d_out, segment_edges=70)):
-            check_mlp(csr, G, xs, xd, w, plan=plan)
+    for hi in (300, 9):  # short rows: scalar lanes
+        csr = _graph(3, 50, 70, 0, hi)
+        G = fg.Graph.from_csr(csr)
+        xs = rng.standard_normal((csr.num_cols, 8)).astype(np.float32)
+        xd = rng.standard_normal((csr.num_rows, 8)).astype(np.float32)
+        for d_out in (5, 37, 67, 130):
+            w = rng.standard_normal((8, d_out)).astype(np.float32)
+            for plan in (None, fg.Plan(G, d_out, segment_edges=70), fg.Plan(G, d_out, segment_edges=4)):
+                check_mlp(csr, G, xs, xd, w, plan=plan)
 
 
 @pytest.mark.parametrize("d", [6, 41, 130, 601])
