@@ -155,6 +155,47 @@ __global__ __launch_bounds__(kBlock) void dense_tile_kernel(const float* x, cons
     }
 }
 
+// Narrow X: one wavefront per 16-row x 64-column tile of Y, four 16 x 16 blocks of
+// v_mfma_f32_16x16x4_f32, every lane loading its operands.  Lane l supplies
+// A[l % 16][l / 16] and B[l / 16][l % 16] and receives D[4 (l / 16) + r][l % 16].
+// Without the staging and its barriers nothing delays the write of Y, and K is
+// padded to 4, not 16.  300,000 rows, us, staged / direct: 8 -> 16: 14.0 / 9.9;
+// 20 -> 7: 19.5 / 14.1; 33 -> 7: 27.9 / 21.8; 100,000 rows, 2 -> 128: 14.2 / 10.4.
+constexpr int kDirectCols = 64;
+
+__global__ __launch_bounds__(kBlock) void dense_direct_kernel(const float* x, const float* w,
+                                                              float* y, int64_t n, int32_t K,
+                                                              int32_t M, int64_t n_tiles) {
+  const int64_t t = wave_item();
+  if (t >= n_tiles) return;
+  const int64_t col_tiles = (M + kDirectCols - 1) / kDirectCols;
+  const int64_t rt = t / col_tiles, ct = t % col_tiles;
+  const int lane = lane_id();
+  const int i = lane & 15, q = lane >> 4;
+  const int64_t arow = rt * 16 + i;
+  f32x4 acc[4] = {};
+  for (int k0 = 0; k0 < K; k0 += 4) {
+    const int k = k0 + q;
+    const float a = (arow < n && k < K) ? x[arow * K + k] : 0.0f;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int64_t col = ct * kDirectCols + b * 16 + i;
+      const float bv = (k < K && col < M) ? w[(int64_t)k * M + col] : 0.0f;
+      acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv, acc[b], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const int64_t col = ct * kDirectCols + b * 16 + i;
+    if (col >= M) continue;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t row = rt * 16 + q * 4 + r;
+      if (row < n) y[row * M + col] = acc[b][r];
+    }
+  }
+}
+
 template <int BM, int BN, int TM, int TN>
 void dense_go(int64_t n, int64_t K, int64_t M, const float* x, const float* w, float* y,
               hipStream_t st) {
@@ -169,6 +210,15 @@ void dense_go(int64_t n, int64_t K, int64_t M, const float* x, const float* w, f
 hipError_t launch_dense_matmul(int64_t n, int64_t K, int64_t M, const float* x, const float* w,
                                float* y, hipStream_t stream) {
   if (n == 0 || M == 0) return hipSuccess;
+  // up to 12 columns of X, or so few in the last step of 16 that the padding
+  // shows (20, 33; 24 and 40 for Y of at most 16 columns, see above)
+  const int64_t pad = (K + kDenseK - 1) / kDenseK * kDenseK - K;
+  if (K <= 12 || (K < 48 && pad >= (M <= 16 ? 8 : 12))) {
+    const int64_t tiles = (n + 15) / 16 * ((M + kDirectCols - 1) / kDirectCols);
+    FG_LAUNCH(dense_direct_kernel, grid_for(tiles, 1), stream, x, w, y, n, (int32_t)K, (int32_t)M,
+              tiles);
+    return hipGetLastError();
+  }
   // 64 x 128 tiles read X half as often as 64 x 64 ones (232,965 rows, 256 ->
   // 128: 171 against 184 us) once they give each of the 256 compute units four
   // or more; below that (20,000 rows, 256 -> 256: 36 against 31 us), and for Y
