@@ -140,8 +140,11 @@ __device__ __forceinline__ void spmm_store(const SpmmParams& p, const Item& it, 
 // WIDE (two or more lane groups, positional ids, one head): 256-edge batches
 // whose ids (and weights) arrive four per lane in one 16-byte load (a quarter
 // of the id loads for the address unit) and go to the group-major LDS table.
-// Without weights, one float4 a lane is held to 7 wavefronts per SIMD (72 registers): the
-// max kernel otherwise takes 85 (5 wavefronts), with no spill either way.
+// Without weights, one float4 a lane is held to 7 wavefronts per SIMD (72
+// registers): the max kernel otherwise takes 85 (5 wavefronts), without a spill
+// either way, and the DUP forms spill 1 to 3 registers.  The copy sums of 64-edge
+// batches fit 64 registers (8 wavefronts), where the compiler left alone takes 70
+// for a plan's items (400K edges in rows of 4, 64 floats: 30.7 -> 28.7 us).
 //
 // DUP (wide batches): graphs that repeat many edges.  Copies of an edge are
 // neighbours in a row, so each batch is packed to one entry per run of equal
@@ -151,7 +154,7 @@ __device__ __forceinline__ void spmm_store(const SpmmParams& p, const Item& it, 
 // gathers: weighted sum 2224 -> 2002 us, max 2202 -> 1997.
 template <int G, int NV, int U, bool MUL, bool MAX, bool EIDS, bool SEG, bool ADD, int HM,
           bool WIDE, bool RAG, bool DUP = false>
-__global__ __launch_bounds__(kBlock, (WIDE && !MUL && NV == 1) ? 7 : 1) void spmm_fast_kernel(SpmmParams p) {
+__global__ __launch_bounds__(kBlock, (MUL || NV > 1) ? 1 : WIDE ? 7 : MAX ? 1 : 8) void spmm_fast_kernel(SpmmParams p) {
   constexpr int NG = kWave / G;
   constexpr bool POS = MAX && !EIDS;
   constexpr bool TAB = MUL && HM == kHeadTable;
