@@ -1403,6 +1403,13 @@ fg_status fg_gsddmm_edge_softmax(const fg_graph* g, int32_t num_heads, int64_t h
                                                          : fg::kTwoPassWholeRowEdges) *
                             std::max<int64_t>(plan->gather.num_segments, 1);
   const bool fused = fg::gsddmm_softmax_fused(num_heads, head_dim, x_src, x_dst);
+  // The weights of calls that the one-pass kernel would have taken, by the item
+  // length or in pieces of its features' slabs, keep its expf; plans of long items
+  // never did (2M uniform edges in rows of 200, 256 floats: 168 us, 179 with it).
+  const bool exact =
+      fused && (!plan || g->num_cols * F * 4 > kDefaultPartitionBytes / 2 ||
+                g->nnz < fg::kTwoPassWholeRowEdges *
+                             std::max<int64_t>(plan->gather.num_segments, 1));
   if (!long_items && fused)
     return from_hip(fg::launch_gsddmm_softmax(gv, plan ? &plan->gather : nullptr, F, x_src, x_dst,
                                               apply_leaky_relu != 0, negative_slope, scores, out,
@@ -1412,7 +1419,7 @@ fg_status fg_gsddmm_edge_softmax(const fg_graph* g, int32_t num_heads, int64_t h
                                    x_dst, scores, hs);
   if (e != hipSuccess) return FG_ERR_HIP;
   return from_hip(fg::launch_edge_softmax(gv, plan ? &plan->plain : nullptr, num_heads, scores,
-                                          apply_leaky_relu != 0, negative_slope, out, fused, hs));
+                                          apply_leaky_relu != 0, negative_slope, out, exact, hs));
 }
 
 fg_status fg_gspmm_max_backward(const fg_graph* g, fg_msg_op msg, int32_t num_heads,
