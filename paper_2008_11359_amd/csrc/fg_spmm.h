@@ -671,8 +671,10 @@ void spmm_fast_seg2(const SpmmParams& prm, bool seg, int64_t avg, dim3 grid, hip
   if constexpr (kWave / G >= 2 && U % 4 == 0 && !EIDS && HM == kOneHead) {
     if (avg >= wide_item_edges<kWave / G>()) {
       // (the sums' run weights cost rows of 64 floats or less what they save: 20M
-      // edges of 32 floats 149 -> 183 us)
-      if constexpr (!RAG && NV == 1 && !(MUL && MAX) && (MAX || G == 32)) {
+      // edges of 32 floats 149 -> 183 us; so does the max's table of first edges up
+      // to 16 floats: communities of 300 edges a row, 8 floats, 109 -> 115 us,
+      // 20M power-law edges of 16 134 -> 137)
+      if constexpr (!RAG && NV == 1 && !(MUL && MAX) && (MAX ? G >= 8 : G == 32)) {
         if (seg && prm.repeats) {
           FG_LAUNCH((spmm_fast_kernel<G, NV, U, MUL, MAX, EIDS, true, ADD, HM, true, RAG, true>),
                     grid, st, prm);
@@ -762,7 +764,10 @@ void spmm_fast_dispatch(const SpmmParams& prm, bool mul, bool seg, int64_t avg, 
     // lanes idle (10M power-law edges, max: 300 floats 754 -> 725 us, 602 2253 ->
     // 1777; weighted sum 701 -> 653, 1585 -> 1478; uniform edges, bound by lines
     // rather than lanes, equal).  16 x 3 for 130-192 floats and 8 x 3 for 66-96
-    // are slower on short rows and equal on long ones.
+    // are slower on short rows and equal on long ones; the max of rows of a few
+    // edges, which leave the second lane group idle, keeps 64 x 2 (4 edges a row, 300
+    // floats 109 us, with 32 x 3 124).
+    else if (MAX && Q > 64 && Q <= 96 && avg < 8) go(SpmmLayout<64, 2, 4, RAG, MANY>{}, 1);
     else if (Q <= 96) go(SpmmLayout<32, 3, 4, RAG, MANY>{}, 1);
     else if (Q <= 128) go(SpmmLayout<64, 2, 4, RAG, MANY>{}, 1);
     else if (Q <= 192) go(SpmmLayout<64, 3, 2, RAG, MANY>{}, 1);
