@@ -1112,6 +1112,7 @@ fg_status fg_plan_create(const fg_graph* g, const int32_t* indptr_host,
     v->ws_width = ws_width;
     v->repeats = repeats;
   }
+  p->gather.shortened = o.auto_gather && gather.S < kDefaultSegmentEdges;
   p->plain.longest_row = o.auto_plain ? 0 : INT64_MAX;
   for (int64_t r = 0; r < g->num_rows; ++r) {
     const int64_t deg = (int64_t)ip[r + 1] - ip[r];
