@@ -210,10 +210,16 @@ void dense_go(int64_t n, int64_t K, int64_t M, const float* x, const float* w, f
 hipError_t launch_dense_matmul(int64_t n, int64_t K, int64_t M, const float* x, const float* w,
                                float* y, hipStream_t stream) {
   if (n == 0 || M == 0) return hipSuccess;
-  // up to 12 columns of X, or so few in the last step of 16 that the padding
-  // shows (20, 33; 24 and 40 for Y of at most 16 columns, see above)
+  // many rows, and up to 12 columns of X (unless much of the last block of 64
+  // columns of Y is padding: 937,000 rows, 8 -> 68, lose 10 us) or a last step of
+  // 16 that mostly is (17, 20, 33; any for Y of at most 16 columns); fewer rows
+  // end together, staged or not
   const int64_t pad = (K + kDenseK - 1) / kDenseK * kDenseK - K;
-  if (K <= 12 || (K < 48 && pad >= (M <= 16 ? 8 : 12))) {
+  const int64_t cols = (M + kDirectCols - 1) / kDirectCols * kDirectCols;
+  const bool narrow = K <= 12   ? M <= kDirectCols || 10 * cols <= 13 * M
+                      : M <= 16 ? K < 64 && pad > 0
+                                : K < 40 && pad >= 12;
+  if (n >= 65536 && narrow) {
     const int64_t tiles = (n + 15) / 16 * ((M + kDirectCols - 1) / kDirectCols);
     FG_LAUNCH(dense_direct_kernel, grid_for(tiles, 1), stream, x, w, y, n, (int32_t)K, (int32_t)M,
               tiles);

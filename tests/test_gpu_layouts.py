@@ -108,9 +108,9 @@ def test_ragged_tail_infinities(d):
 
 @pytest.mark.parametrize("n,d_in,d_out", [(1, 15, 3), (63, 16, 63), (64, 17, 64), (65, 33, 65),
                                           (129, 32, 128), (200, 31, 129), (70405, 17, 65),
-                                          (70405, 3, 130), (35300, 48, 256), (1, 1, 1), (17, 12, 65),
-                                          (200, 13, 64), (129, 20, 130), (129, 21, 130),
-                                          (70405, 33, 7), (100, 24, 16), (100, 24, 17)])
+                                          (70405, 3, 130), (35300, 48, 256), (1, 1, 1), (65537, 12, 64),
+                                          (65536, 13, 3), (70001, 5, 100), (70001, 8, 129),
+                                          (70405, 33, 7), (65549, 24, 16), (65549, 40, 1)])
 def test_dense_tiles(n, d_in, d_out):
     """Tile and step edges of the matrix-core transform; from 1024 tiles of
     64 x 128 on its wider tiles, and few columns of X without staging."""
