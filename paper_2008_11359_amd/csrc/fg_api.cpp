@@ -462,6 +462,10 @@ int64_t piece_cost(const int32_t* ip, int64_t num_rows, int32_t S, int64_t cap, 
   int64_t n = 0, longest = 0;
   for (int64_t r = 0; r < num_rows; ++r) {
     const int64_t deg = (int64_t)ip[r + 1] - ip[r];
+    if (deg <= S && (band_rows < 0 || deg <= band_rows)) {  // most rows
+      longest = std::max(longest, deg);
+      continue;
+    }
     const int64_t k = row_pieces(deg, S, cap, band_rows);
     if (k >= 2) n += k;
     longest = std::max(longest, (deg + k - 1) / k);
@@ -961,10 +965,15 @@ fg_status upload(fg_plan* p, const Schedule& sc, fg::PlanView& v, hipStream_t hs
   // plain schedule's order by length class); any other order keeps every item
   // in the first group
   int64_t nl = 0, nn = 0, nm = 0;
+  int64_t edges = 0;
+  double squares = 0.0;
   bool ordered = true, short_whole = true, medium_whole = true;
   int prev = INT32_MAX;
   for (const fg::Seg& sg : sc.segs) {
     const int64_t len = (int64_t)sg.end - sg.begin;
+    v.longest_item = std::max(v.longest_item, len);
+    edges += len;
+    squares += (double)len * (double)len;
     const int cls = len_class(len);
     if (sg.row < 0 || cls > prev) ordered = false;
     prev = cls;
@@ -979,6 +988,7 @@ fg_status upload(fg_plan* p, const Schedule& sc, fg::PlanView& v, hipStream_t hs
   v.num_nonempty = ordered ? nn : v.num_segments;
   v.num_long = (ordered && short_whole) ? nl : v.num_nonempty;
   v.num_medium = (ordered && short_whole && medium_whole) ? nm : v.num_long;
+  v.edge_mean = (int64_t)(squares / (double)std::max<int64_t>(edges, 1));
   v.num_split_rows = (int64_t)sc.fix.size();
   v.num_slots = (int64_t)sc.slot_fix.size();
   return FG_OK;
