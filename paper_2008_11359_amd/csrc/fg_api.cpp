@@ -322,6 +322,12 @@ constexpr int64_t kInfinityCacheBytes = int64_t(256) << 20;
 constexpr int64_t kShareItems = 2048, kSlotEdges = 70, kMergeEdges = 60;
 // Longer pieces than that default only if they save this share of its cost.
 constexpr double kPieceGain = 0.1;
+// The gathers of these graphs miss the dies' L2s.  Features of up to kNearBytes
+// stay in them, and there more wavefronts pay for the merge unless rows are long
+// and many (whole / in default pieces, us: scores of 1,496 rows of 143 edges, 213
+// floats 27 / 20; max and its gradient, 1,155 of 280, 409 floats 115 / 81; sum of
+// 3,000 of 800, 128 floats 41 / 46).
+constexpr int64_t kNearBytes = 8 << 20, kNearRows = 2048, kNearRowEdges = 512;
 
 struct Options {
   bool auto_gather, auto_plain;  // piece lengths chosen here, not by the caller
@@ -822,7 +828,13 @@ fg_status make_schedules(const int32_t* ip, const int32_t* ix, int64_t num_rows,
         band = std::min<int64_t>((max_deg + o.S_whole - 1) / o.S_whole, o.cap) >= kXcds;
       }
       const int64_t band_rows = band ? o.band_rows : -1;
-      og.S = o.auto_gather ? settle_default(ip, num_rows, o.S, o.S_whole, o.cap, band_rows) : o.S;
+      int64_t rows = 0;  // with edges
+      for (int64_t r = 0; r < num_rows; ++r) rows += ip[r + 1] > ip[r];
+      const bool near = num_cols * o.max_width * 4 <= kNearBytes &&
+                        (rows < kNearRows || ip[num_rows] < kNearRowEdges * rows);
+      og.S = o.auto_gather && !near
+                 ? settle_default(ip, num_rows, o.S, o.S_whole, o.cap, band_rows)
+                 : o.S;
       og.S = settle_segment(ip, num_rows, og, band_rows);
       if (op.S == og.S && band_rows < 0) {
         gather = plain;

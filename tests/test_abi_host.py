@@ -777,13 +777,18 @@ def test_sddmm_schedule_needs_long_rows(deg, own):
 def test_balanced_rows_stay_whole(n, deg):
     """Where a few thousand rows of about equal length share the edges, pieces
     of 1/4096 of them would cut nearly every row, and the merge costs more than
-    they give; one long row among them is still cut, and so are few rows."""
+    they give, if the features (20 MB here) miss the L2s or rows are many and
+    long; one long row among them is still cut, and so are few rows."""
+    m = 40000
     ptr = (np.arange(n + 1) * deg).astype(np.int32)
+    kw = dict(num_cols=m, max_width=128)
     for which in ("gather", "plain"):
-        assert fg.schedule_host(ptr, max_width=128, which=which)[1:] == (0, 0)
+        assert fg.schedule_host(ptr, which=which, **kw)[1:] == (0, 0)
+    near = fg.schedule_host(ptr, num_cols=n, max_width=128)[1]
+    assert near == (0 if n >= 2048 and deg >= 512 else n if deg * n // 4096 < deg else 0)
     ptr[n // 2:] += 40 * deg
     for which in ("gather", "plain"):
-        segs, split, slots = fg.schedule_host(ptr, max_width=128, which=which)
+        segs, split, slots = fg.schedule_host(ptr, which=which, **kw)
         assert split >= 1 and (segs[:, 2] - segs[:, 1]).max() <= 10 * deg
     few = (np.arange(251) * 1600).astype(np.int32)
-    assert fg.schedule_host(few, max_width=128)[1] == 250
+    assert fg.schedule_host(few, **kw)[1] == 250
