@@ -115,15 +115,20 @@ typedef struct fg_graph {
  *  - plain (edge softmax): rows with more than S edges are cut into
  *    k = min(ceil(deg / S), max_row_segments) equal segments, S =
  *    softmax_segment_edges if given, else segment_edges if given, else 16384,
- *    or nnz / 4096 on smaller graphs (at least 512)
+ *    or nnz / 4096 on smaller graphs (at least 512; longer where that costs a
+ *    tenth less by the longest piece against the number of partial results, so
+ *    that rows of about equal length stay whole; launches whose longest row has
+ *    at most 4096 / H edges take the rows whole)
  *    (a whole row of up to 16384 scores is streamed by one wavefront; a cut
  *    row is read once more by a merge pass); long items first
  *    (fg_plan_options.item_order), rows without edges last;
  *  - gather (gSpMM, gSDDMM, the fused SDDMM + edge softmax, fused
  *    attention): as plain with S =
  *    segment_edges if given, else 1536, or nnz / 4096 on smaller graphs (at
- *    least 128 and 16384 / max_width, and longer where fg_gspmm_noalloc's
- *    scratch would hold fewer widths than at 1536), unless source
+ *    least 128 and 16384 / max_width, and longer where that costs a tenth less,
+ *    as above, unless num_cols x max_width features take 8 MiB or less and rows
+ *    are fewer than 2048 or shorter than 512 edges on average; and longer where
+ *    fg_gspmm_noalloc's scratch would hold fewer widths than at 1536), unless source
  *    partitioning applies (by default once the num_cols x max_width source
  *    features exceed 256 MiB, the Infinity Cache, or 32 MiB when the
  *    gathers are spread; see fg_plan_options.source_slab_rows).  With it,
@@ -382,12 +387,13 @@ fg_status fg_gat_aggregate(const fg_graph* g, int32_t num_heads, int64_t head_di
  * Eq. 4 and their normalisation, fused where the scores are produced, as the
  * paper fuses UDFs into its templates, Sec. III-B):
  *   scores[e, h] = fg_gsddmm's output;  out[e, h] = fg_edge_softmax(scores)
+ * (out up to the rounding of its exponentials)
  * One head with dh % 4 == 0, dh <= 1024 and 16-byte aligned features runs as
  * one pass (plus the merge of split rows), unless the plan's items average
- * 56 edges or more (128 without split rows): there, and for other shapes, the two operators run one
- * after the other (the SDDMM's batches of 256 edges and the streaming softmax
- * are faster on such plans than the fused pass).  Both arrays are [nnz_total, H], written for
- * the edges of g.  A plan must have max_width >= max(H * dh, H).
+ * 56 edges or more (128 without split rows): there, and for other shapes, the
+ * two operators run one after the other (the SDDMM's batches of 256 edges and
+ * the streaming softmax are faster on such plans than the fused pass).  Both
+ * arrays are [nnz_total, H], written for the edges of g.  A plan must have max_width >= max(H * dh, H).
  * ------------------------------------------------------------------------- */
 fg_status fg_gsddmm_edge_softmax(const fg_graph* g, int32_t num_heads, int64_t head_dim,
                                  const float* x_src, const float* x_dst, int32_t apply_leaky_relu,

@@ -284,7 +284,8 @@ class Plan:
     than ``segment_edges`` (default 1536 edges in the gather schedule of
     gSpMM / gSDDMM, 16,384 in the edge-softmax schedule, which
     ``softmax_segment_edges`` sets apart; about 1/4096 of the edges on graphs
-    of fewer than 6.3 or 67 million) are cut into equal pieces (at most
+    of fewer than 6.3 or 67 million, longer where rows of about equal length
+    would be cut to no use) are cut into equal pieces (at most
     ``max_row_segments``); long rows of the gather schedule may also be cut
     at source-slab boundaries, so that each die gathers from a narrow band of
     the features.  ``source_slab_rows``: 0 (default) automatic slabs once the
